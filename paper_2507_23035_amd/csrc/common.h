@@ -228,9 +228,9 @@ hipError_t launch_gemm_percol(const GemmArgs& a, hipStream_t s);
 // Y (+)= Y* + Y' in one launch when a.n <= kFusedMaxTokens.
 constexpr int kFusedMaxTokens = 32;
 hipError_t launch_compensate(const CompArgs& a, hipStream_t s);
-// Row-layout lists (a.idx_w as below) on the matrix cores, and whether its
-// grid suits the size
-bool compensate_mm_fits(int n, int d_out);
+// Row-layout lists (a.idx_w as below) on the matrix cores, and whether that is
+// the faster kernel (per, rounds: tokens a wave and rounds of k_compensate_wr)
+bool compensate_mm_fits(int n, int d_out, int k, int per, long rounds);
 hipError_t launch_compensate_mm(const CompArgs& a, hipStream_t s);
 // GEMM-layout lists of many tokens with per-column codebooks (fp16 [d_out][16])
 hipError_t launch_compensate_percol(const CompArgs& a, const uint16_t* cb_cols, hipStream_t s);

@@ -485,13 +485,15 @@ hipError_t launch_compensate_wr(const CompArgs& a, hipStream_t s) {
     if (a.accumulate) return hipSuccess;
     return launch_fill_zero(a.y, (size_t)a.n * a.d_out, s);
   }
-  if (compensate_mm_fits(a.n, a.d_out)) return launch_compensate_mm(a, s);
   const int wn = (a.d_out + 7) / 8;
   // tokens per tile: every wave's lists fit its LDS area at once (one copy,
   // no pipeline drain) when 2k <= WR_C / 8 ... WR_C; at most 8 per wave
-  const int E = 2 * a.k;
-  const int tt = WR_W * max(1, min(8, WR_C / E));
+  const int E = 2 * a.k, per = max(1, min(8, WR_C / E)), tt = WR_W * per;
   const int nslab = (wn + 63) / 64, ntile = (a.n + tt - 1) / tt;
+  const long rounds = ((long)nslab * ntile + device_cus() - 1) / device_cus();
+  // (compacted lists have few entries of the 2k)
+  if (a.cnt || compensate_mm_fits(a.n, a.d_out, a.k, per, rounds))
+    return launch_compensate_mm(a, s);
   const size_t lds = 8 * WR_W * WR_C;  // dynamic part: the lists
   hipError_t e = hipFuncSetAttribute((const void*)k_compensate_wr,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);

@@ -5,9 +5,10 @@ lane, lists longer than a wave's registers, and per-column codebooks with the
 GEMM before it (more than 96 tokens).  And the split by channel where it is
 taken, i.e. past 10^9 list entries x columns.
 
-Bound: a sum of 2k products r * c, r held as an fp16 pair to 2^-25 of the
-token's largest residual, summed in fp32: (2k + 2) 2^-24 sum |r c| from the
-sum and 2^-25 max |r| sum |c| from the pair, times s_j; twice that is allowed."""
+Bound: a sum of 2k products r * c in fp32: (2k + 2) 2^-24 sum |r c|, times
+s_j; twice that is allowed.  The split's heavy channels hold r over the token's
+scale as an fp16 pair, whose low half ends in the subnormals: 2^-25 max |r|
+sum |c| more."""
 import numpy as np
 import pytest
 
@@ -29,7 +30,7 @@ CASES = [
 ]
 
 
-def reference(mx, mn, r, w, s_w):
+def reference(mx, mn, r, w, s_w, pair=False):
     ch = np.concatenate([mx, mn], 1)
     n, d_in = ch.shape[0], w.shape[0]
     dense = np.zeros((n, d_in))
@@ -39,7 +40,7 @@ def reference(mx, mn, r, w, s_w):
     ref = (torch.from_numpy(dense) @ torch.from_numpy(w)).numpy() * s_w
     mag = (torch.from_numpy(np.abs(dense)) @ torch.from_numpy(np.abs(w))).numpy() * s_w
     rest = np.abs(r).max(1, keepdims=True) * np.abs(w).max() * ch.shape[1] * s_w
-    return ref, 2.0 * ((ch.shape[1] + 2) * 2.0 ** -24 * mag + 2.0 ** -25 * rest)
+    return ref, 2.0 * ((ch.shape[1] + 2) * 2.0 ** -24 * mag + (2.0 ** -25 * rest if pair else 0.0))
 
 
 def inputs(n, d_in, d_out, k):
@@ -85,6 +86,50 @@ def test_compensate_rows(n, d_in, d_out, k):
     lists = [upload(v) for v in lists]
     check(lambda y, acc: oasis.outlier_compensate_rows(*lists, idx_wr, lut, 4, ts, d_in, y=y,
                                                        accumulate=acc), ref, bound, n, d_out)
+
+
+@pytest.mark.parametrize("n,d_in,d_out,k", [
+    (33, 256, 100, 4),        # 6 waves a task
+    (500, 264, 4100, 9),      # fewer
+    (1100, 2048, 5000, 100),  # one, compacted lists of the split by channel
+])
+def test_small_entries_beside_a_massive_one(n, d_in, d_out, k):
+    """A token's small entries stay as they are beside one of 2^20 to 2^34 times
+    their size: where that one meets a centroid of 0 the column is their sum alone.
+    The bound is that of the fp32 sum, with no term for the residuals' format."""
+    w_idx, cb, s_w, mx, mn, r = inputs(n, d_in, d_out, k)
+    rng = np.random.default_rng(k)
+    mx[mx < 16] += 16                      # (a channel may occur twice)
+    mn[(mn >= 0) & (mn < 16)] += 16
+    mx[:, 1] = rng.integers(0, 16, n)      # the massive entry's channel
+    r = (rng.standard_normal((n, 2 * k)) * np.exp2(rng.uniform(-14, 0, (n, 2 * k)))).astype(np.float32)
+    r[:, 1] = rng.choice([-1.0, 1.0], n) * 2.0 ** 20
+    cb[7] = 0.0
+    w_idx[:16, ::3] = 7
+    split = n * 2 * k * d_out > 10 ** 9
+    print(f"case compensate_mm range n={n} d_in={d_in} d_out={d_out} k={k} split={split}", flush=True)
+    w = cb.astype(np.float64)[w_idx]
+    ch = np.concatenate([mx, mn], 1)
+    dense, absd = np.zeros((n, d_in)), np.zeros((n, d_in))
+    for i in range(n):
+        ok = ch[i] >= 0
+        np.add.at(dense[i], ch[i][ok], r[i][ok].astype(np.float64))
+        np.add.at(absd[i], ch[i][ok], np.abs(r[i][ok].astype(np.float64)))
+    ref = (torch.from_numpy(dense) @ torch.from_numpy(w)).numpy() * s_w.astype(np.float64)
+    mag = (torch.from_numpy(absd) @ torch.from_numpy(np.abs(w))).numpy() * s_w.astype(np.float64)
+    bound = 2.0 * (2 * k + 2) * 2.0 ** -24 * mag
+    assert 0.0 < np.median(np.abs(ref[:, ::3])) < 2.0 ** 8   # the columns in question
+    lut = oasis.build_lut(np.arange(16).astype(np.float16), 4, cb, 4)
+    idx_wr, idx_w = upload(oasis.pack_weight_rows(w_idx).view(np.int32)), upload(
+        oasis.pack_weight_indices(w_idx).view(np.int32))
+    lists, ts = [upload(v) for v in (mx, mn, r)], upload(s_w)
+    codes = torch.zeros((n, d_in // 2), dtype=torch.uint8, device="cuda:0")
+    t = torch.zeros(n, device="cuda:0")    # Y* = 0
+    args = (codes, t, idx_w, idx_wr, ts, lut, 4, 4, *lists)
+    y = (oasis.lut_gemm_compensated_split if split else oasis.lut_gemm_compensated_rows)(*args)
+    torch.cuda.synchronize()
+    err = np.abs(y.cpu().numpy().astype(np.float64) - ref)
+    assert np.all(err <= bound), np.max(err / (bound + 1e-300))
 
 
 @pytest.mark.parametrize("n,d_in,d_out,k", [(33, 256, 100, 4), (800, 256, 6700, 3)])
@@ -180,7 +225,8 @@ def test_split_is_taken(n, d_in, d_out, k, mode):
     torch.cuda.synchronize()
     w = L.cb_w.astype(np.float64)[L.w_idx]
     a = L.cb_a.astype(np.float64)[q["a"]] * q["t"].astype(np.float64)[:, None]
-    comp, bound = reference(q["max_idx"], q["min_idx"], q["residual"], w, L.s_w.astype(np.float64))
+    comp, bound = reference(q["max_idx"], q["min_idx"], q["residual"], w, L.s_w.astype(np.float64),
+                            pair=True)
     main = (torch.from_numpy(a) @ torch.from_numpy(w)).numpy() * L.s_w
     mag = (torch.from_numpy(np.abs(a)) @ torch.from_numpy(np.abs(w))).numpy() * L.s_w
     bound = bound + 2.0 * (d_in + 2) * 2.0 ** -24 * mag
