@@ -123,7 +123,13 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) k_gemm_mfma_ks(GemmArgs A, in
   };
 
   const uint32_t l4w = (uint32_t)r32 * 4u, l4a = l4w + 128u;
-  float16_t acc[CW][FT];
+  // PERCOL: two sums an output, for the steps in turn.  A wave's chain of d_in /
+  // (16 NW) MFMAs is what its rounding error grows with: against 64 bits one
+  // chain was off by 1.6e-7 at 4096 channels and 2.3e-7 at 11008, the GEMV
+  // launches that this tile replaced (chains of d_in / 512) by 1.4e-7 and
+  // 1.8e-7, two chains by 1.3e-7 and 1.75e-7; the time grows by under 2 %
+  constexpr int NA = PERCOL ? 2 : 1;
+  float16_t acc[NA][CW][FT];
   // operands of step st of block blk
   auto operands = [&](const KsCodes<CW, FT>& kc, int blk, int st, half8_t (&a)[CW],
                       half8_t (&b)[FT]) {
@@ -138,12 +144,13 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) k_gemm_mfma_ks(GemmArgs A, in
 #pragma unroll
     for (int f = 1; f < FT; ++f) bop(f);
   };
-  auto mma = [&](const half8_t (&a)[CW], const half8_t (&b)[FT]) {
+  auto mma = [&](const half8_t (&a)[CW], const half8_t (&b)[FT], int st) {
+    auto& s = acc[st % NA];
 #pragma unroll
     for (int f = 0; f < FT; ++f)
 #pragma unroll
       for (int c = 0; c < CW; ++c)
-        acc[c][f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[c], b[f], acc[c][f], 0, 0, 0);
+        s[c][f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[c], b[f], s[c][f], 0, 0, 0);
   };
   constexpr int NM = CW * FT;                   // MFMAs per step
   constexpr int PX = (4 * (CW + FT) + NM - 1) / NM;  // perms (= table reads) per MFMA
@@ -163,24 +170,24 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) k_gemm_mfma_ks(GemmArgs A, in
 #pragma unroll
     for (int st = 0; st < 4; ++st) {
       operands(kc, blk, st, a0, b0);
-      mma(a0, b0);
+      mma(a0, b0, st);
     }
   };
   // one block; a0 / b0 hold its step 0 operands on entry and those of the
   // wave's next block (in nxt) on exit
   auto pipe_block = [&](KsCodes<CW, FT>& cur, const KsCodes<CW, FT>& nxt, int blk) {
     operands(cur, blk, 1, a1, b1);
-    mma(a0, b0);
+    mma(a0, b0, 0);
     interleave(false);
     operands(cur, blk, 2, a0, b0);
-    mma(a1, b1);
+    mma(a1, b1, 1);
     interleave(false);
     operands(cur, blk, 3, a1, b1);
-    mma(a0, b0);
+    mma(a0, b0, 2);
     interleave(false);
     operands(nxt, blk + NW, 0, a0, b0);
     load(blk + 2 * NW, cur);
-    mma(a1, b1);
+    mma(a1, b1, 3);
     interleave(true);
   };
 
@@ -219,11 +226,13 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) k_gemm_mfma_ks(GemmArgs A, in
   const bool vec = (d_out & 3u) == 0 && (reinterpret_cast<uintptr_t>(A.y) & 15u) == 0;
   for (int u = blockIdx.x; u < T; u += gridDim.x) {
 #pragma unroll
-    for (int c = 0; c < CW; ++c)
+    for (int s = 0; s < NA; ++s)
 #pragma unroll
-      for (int f = 0; f < FT; ++f)
+      for (int c = 0; c < CW; ++c)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[c][f][v] = 0.0f;
+        for (int f = 0; f < FT; ++f)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[s][c][f][v] = 0.0f;
     if constexpr (PIPE) {
       operands(buf[0], wave, 0, a0, b0);
       int blk = wave;
@@ -277,11 +286,17 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) k_gemm_mfma_ks(GemmArgs A, in
             for (int c = 0; c < CW; ++c) a[c] = expand_dual(vw[st][c], tb, l4w);
 #pragma unroll
             for (int f = 0; f < FT; ++f) b[f] = __builtin_bit_cast(half8_t, va[st][f]);
-            mma(a, b);
+            mma(a, b, 0);
             hload(hb + NW, st);
           }
         }
       }
+    }
+    if constexpr (NA > 1) {
+#pragma unroll
+      for (int c = 0; c < CW; ++c)
+#pragma unroll
+        for (int f = 0; f < FT; ++f) acc[0][c][f] += acc[1][c][f];
     }
     const int jt = j0, tt = t0;
     const float scu = scl;
@@ -309,8 +324,8 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) k_gemm_mfma_ks(GemmArgs A, in
         for (int q = 0; q < 4; ++q) {
           const int x = 2 * q + h;
           red[(wave * PT + t) * 256 + 32 * x + (r32 ^ x)] =
-              float4_t{acc[c][f][4 * q], acc[c][f][4 * q + 1], acc[c][f][4 * q + 2],
-                       acc[c][f][4 * q + 3]};
+              float4_t{acc[0][c][f][4 * q], acc[0][c][f][4 * q + 1], acc[0][c][f][4 * q + 2],
+                       acc[0][c][f][4 * q + 3]};
         }
       }
       __syncthreads();

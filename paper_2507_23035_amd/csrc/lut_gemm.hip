@@ -1402,9 +1402,13 @@ static void launch_gemv_percol(const GemmArgs& a, hipStream_t s) {
 // Up to 96 tokens: one GEMV launch per 32-token chunk (token-major arguments
 // offset to the chunk); every chunk re-reads the weight codes, from the
 // last-level cache when they fit there.  More: the GEMM with the reduction
-// split over a workgroup's waves, then the compensation added to it (512 x 4096
-// x 4096, k = 32: 171 us in 16 GEMV launches, 36 + 31 us so; at 70 x 4096 x 4096
-// without lists three launches take 16.8 us, the GEMM 15.3).
+// split over a workgroup's waves, then the compensation added to it, which
+// take about the same time for 33 tokens as for 128.  Three launches and that
+// meet at 96 tokens of 4096 x 4096, k = 32 (27.8 and 30.6 us); past 96 the
+// fourth launch makes it the faster one at every size tried (us at 97 tokens,
+// launches and GEMM: 4096 x 512 31 and 23, 11008 x 512 61 and 42, 4096 x 4096
+// 33 and 31, 1024 x 4096 23 and 18, 4096 x 11008 89 and 57, 11008 x 4096 64 and
+// 62, 8192 x 28672 333 and 183; 512 x 4096 x 4096 171 and 67).
 hipError_t launch_gemm_percol(const GemmArgs& a, hipStream_t s) {
   if (a.n > 96) {
     const hipError_t e = launch_gemm_ks_percol(a, s);

@@ -198,6 +198,34 @@ def test_percol_many_tokens(n, d_in, d_out, k):
           n, d_out)
 
 
+@pytest.mark.parametrize("n,d_in,d_out,k", [(128, 4096, 512, 32), (100, 11008, 320, 88)])
+def test_percol_error_of_one_gemm(n, d_in, d_out, k):
+    """One call past 96 tokens is no further from 64 bits than calls of 32 tokens
+    (2-norms over 30000 and more outputs, whose ratio is steady to a few per cent)."""
+    print(f"case percol error n={n} d_in={d_in} d_out={d_out} k={k}", flush=True)
+    L = synth.make_layer(synth.custom(n, d_in, d_out, k, seed=n))
+    cols = synth.percol_codebooks(L)
+    q = O.quantize_act(L.x, L.cb_a, 4, k)
+    w = np.take_along_axis(cols.astype(np.float64).T, L.w_idx.astype(np.int64), axis=0)
+    a = L.cb_a.astype(np.float64)[q["a"]] * q["t"].astype(np.float64)[:, None]
+    s_w = L.s_w.astype(np.float64)
+    ref = (torch.from_numpy(a) @ torch.from_numpy(w)).numpy() * s_w
+    ref += reference(q["max_idx"], q["min_idx"], q["residual"], w, s_w)[0]
+    lut = oasis.build_lut(L.cb_a, 4, L.cb_w, 4)
+    idx_w, ts = upload(oasis.pack_weight_indices(L.w_idx).view(np.int32)), upload(L.s_w)
+    act, t, cb = upload(O.pack_act_indices(q["a"])), upload(q["t"]), upload(cols)
+    lists = [upload(q[key]) for key in ("max_idx", "min_idx", "residual")]
+
+    def error(step):
+        y = torch.cat([oasis.lut_gemm_compensated_percol(act[i:i + step], t[i:i + step], idx_w, ts,
+                                                         lut, cb, 4, 4, *(v[i:i + step] for v in lists))
+                       for i in range(0, n, step)])
+        return np.linalg.norm(y.cpu().numpy().astype(np.float64) - ref) / np.linalg.norm(ref)
+
+    one, launches = error(n), error(32)
+    assert one <= 1.05 * launches, (one, launches)
+
+
 @pytest.mark.parametrize("n,d_in,d_out,k,mode", [
     (2000, 256, 4000, 64, O.SCALE_NONE),    # residuals over t past 2^15 leave the GEMM
     (1100, 1088, 2000, 256, O.SCALE_ABSMAX),  # more heavy channels than the dense part takes
