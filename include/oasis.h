@@ -257,7 +257,7 @@ int oasis_outlier_compensate(const int32_t* max_idx, const int32_t* min_idx, con
  *            codes of input channel p for output columns 8m..8m+7, column
  *            8m+c in bits 4c..4c+3 (zero past d_out).
  *   Every other argument, the result and accumulate as in
- *   oasis_outlier_compensate (fp32 sums, their order depends on the sizes).
+ *   oasis_outlier_compensate (sums in list order per output).
  * Errors: NULL, SHAPE, BITS, K, ALIGN, TOO_LARGE (d_in * ceil(d_out/8) * 4
  * >= 2^31), LAUNCH.
  */

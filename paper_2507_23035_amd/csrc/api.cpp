@@ -372,7 +372,7 @@ static int gemm_compensated(const uint8_t* idx_act, const float* act_scale, int 
   if (e != hipSuccess || k == 0) return launched(e);
   oasis::CompArgs c{max_idx, min_idx, residual, n, k, idx_wr ? idx_wr : idx_w, lut, b_w,
                     w_scale, d_in, d_out, y, 1};
-  return launched(idx_wr ? oasis::launch_compensate_wr(c, stream)
+  return launched(idx_wr ? oasis::launch_compensate_lists(c, stream)
                          : oasis::launch_compensate(c, stream));
 }
 

@@ -234,8 +234,10 @@ bool compensate_mm_fits(int n, int d_out, int k, int per, long rounds);
 hipError_t launch_compensate_mm(const CompArgs& a, hipStream_t s);
 // GEMM-layout lists of many tokens with per-column codebooks (fp16 [d_out][16])
 hipError_t launch_compensate_percol(const CompArgs& a, const uint16_t* cb_cols, hipStream_t s);
-// Same, with idx_w in the row layout (uint32 [d_in][ceil(d_out / 8)]).
+// Same, with idx_w in the row layout (uint32 [d_in][ceil(d_out / 8)]): summed in
+// list order, or by the faster kernel for the size in an order of its own.
 hipError_t launch_compensate_wr(const CompArgs& a, hipStream_t s);
+hipError_t launch_compensate_lists(const CompArgs& a, hipStream_t s);
 hipError_t launch_fill_zero(float* y, size_t count, hipStream_t s);
 
 }  // namespace oasis

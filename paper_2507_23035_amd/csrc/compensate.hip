@@ -479,21 +479,20 @@ __global__ void __launch_bounds__(64 * WR_W) k_compensate_wr(CompArgs A, int wn,
   }
 }
 
+// tokens per wave and tile of k_compensate_wr: every wave's lists fit its LDS
+// area at once (one copy, no pipeline drain) when 2k <= WR_C / 8 ... WR_C; at
+// most 8 per wave
+static int wr_tokens(int k) { return max(1, min(8, WR_C / (2 * k))); }
+
+// in list order
 hipError_t launch_compensate_wr(const CompArgs& a, hipStream_t s) {
   if (a.n == 0 || a.d_out == 0) return hipSuccess;
   if (a.k == 0) {
     if (a.accumulate) return hipSuccess;
     return launch_fill_zero(a.y, (size_t)a.n * a.d_out, s);
   }
-  const int wn = (a.d_out + 7) / 8;
-  // tokens per tile: every wave's lists fit its LDS area at once (one copy,
-  // no pipeline drain) when 2k <= WR_C / 8 ... WR_C; at most 8 per wave
-  const int E = 2 * a.k, per = max(1, min(8, WR_C / E)), tt = WR_W * per;
+  const int wn = (a.d_out + 7) / 8, tt = WR_W * wr_tokens(a.k);
   const int nslab = (wn + 63) / 64, ntile = (a.n + tt - 1) / tt;
-  const long rounds = ((long)nslab * ntile + device_cus() - 1) / device_cus();
-  // (compacted lists have few entries of the 2k)
-  if (a.cnt || compensate_mm_fits(a.n, a.d_out, a.k, per, rounds))
-    return launch_compensate_mm(a, s);
   const size_t lds = 8 * WR_W * WR_C;  // dynamic part: the lists
   hipError_t e = hipFuncSetAttribute((const void*)k_compensate_wr,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -501,6 +500,18 @@ hipError_t launch_compensate_wr(const CompArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(k_compensate_wr, dim3(nslab * ntile), dim3(64 * WR_W), lds, s, a, wn, nslab,
                      ntile, tt);
   return hipGetLastError();
+}
+
+// in an order of the sizes' choosing
+hipError_t launch_compensate_lists(const CompArgs& a, hipStream_t s) {
+  if (a.n == 0 || a.d_out == 0 || a.k == 0) return launch_compensate_wr(a, s);
+  const int per = wr_tokens(a.k), tt = WR_W * per;
+  const long wgs = (long)((a.d_out + 511) / 512) * ((a.n + tt - 1) / tt);
+  const long rounds = (wgs + device_cus() - 1) / device_cus();
+  // (compacted lists have few entries of the 2k)
+  if (a.cnt || compensate_mm_fits(a.n, a.d_out, a.k, per, rounds))
+    return launch_compensate_mm(a, s);
+  return launch_compensate_wr(a, s);
 }
 
 template <bool PERCOL>

@@ -365,7 +365,7 @@ hipError_t launch_compensate_split(const CompArgs& a, const uint32_t* idx_w_gemm
   if ((e = launch_gemm_values(g, s)) != hipSuccess) return e;
 
   // the rest: y += Y' of the compacted lists
-  return launch_compensate_wr(sparse_args(a, ws, 1), s);
+  return launch_compensate_lists(sparse_args(a, ws, 1), s);
 }
 
 // Main branch and compensation with the heavy channels inside the GEMM: the
@@ -390,7 +390,7 @@ hipError_t launch_gemm_compensated_split(const GemmArgs& g, const CompArgs& a,
   // measured slower: 3.29 vs 2.73 ms at 4096x8192x28672 - four times the
   // activation bytes through L2 for every column tile)
   if ((e = launch_gemm_heavy(m, s)) != hipSuccess) return e;
-  return launch_compensate_wr(sparse_args(a, ws, 1), s);
+  return launch_compensate_lists(sparse_args(a, ws, 1), s);
 }
 
 // ----------------------------------------------------------------------------

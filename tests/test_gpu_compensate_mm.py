@@ -1,6 +1,6 @@
-"""The compensation of many tokens.  Row layout (matrix cores): each number of
-waves per task, remainders in tokens, columns and list positions, lists longer
-than a wave holds, tokens without entries.  GEMM layout: one and four columns a
+"""The compensation of many tokens.  Row layout (on the matrix cores, and in list
+order): each number of waves per task, remainders in tokens, columns and list
+positions, lists longer than a wave holds, tokens without entries.  GEMM layout: one and four columns a
 lane, lists longer than a wave's registers, and per-column codebooks with the
 GEMM before it (more than 96 tokens).  And the split by channel where it is
 taken, i.e. past 10^9 list entries x columns.
@@ -76,16 +76,53 @@ def check(call, ref, bound, n, d_out):
     assert np.all(np.abs(got - ref - 0.5) <= bound + 2.0 ** -23 * (np.abs(ref) + 1.0))
 
 
+def rows_call(fused, lists, w_idx, lut, ts):
+    """Y' from the row layout: the matrix-core kernel through the fused call with
+    tokens of scale 0 (Y* = 0), or the call that sums in list order."""
+    n, (d_in, _) = lists[0].shape[0], w_idx.shape
+    idx_wr = upload(oasis.pack_weight_rows(w_idx).view(np.int32))
+    if not fused:
+        return lambda y, acc: oasis.outlier_compensate_rows(*lists, idx_wr, lut, 4, ts, d_in, y=y,
+                                                            accumulate=acc)
+    idx_w = upload(oasis.pack_weight_indices(w_idx).view(np.int32))
+    codes = torch.zeros((n, d_in // 2), dtype=torch.uint8, device="cuda:0")
+    t = torch.zeros(n, device="cuda:0")
+    return lambda y, acc: oasis.lut_gemm_compensated_rows(codes, t, idx_w, idx_wr, ts, lut, 4, 4,
+                                                          *lists, y=y, accumulate=acc)
+
+
 @pytest.mark.parametrize("n,d_in,d_out,k", CASES)
-def test_compensate_rows(n, d_in, d_out, k):
-    print(f"case compensate_mm n={n} d_in={d_in} d_out={d_out} k={k}", flush=True)
+@pytest.mark.parametrize("fused", [True, False])
+def test_compensate_rows(n, d_in, d_out, k, fused):
+    print(f"case compensate_mm n={n} d_in={d_in} d_out={d_out} k={k} fused={fused}", flush=True)
     w_idx, cb, s_w, mx, mn, r = inputs(n, d_in, d_out, k)
     lut = oasis.build_lut(cb, 4, cb, 4)
-    idx_wr, lists, ts = upload(oasis.pack_weight_rows(w_idx).view(np.int32)), (mx, mn, r), upload(s_w)
     ref, bound = reference(mx, mn, r, cb.astype(np.float64)[w_idx], s_w.astype(np.float64))
-    lists = [upload(v) for v in lists]
-    check(lambda y, acc: oasis.outlier_compensate_rows(*lists, idx_wr, lut, 4, ts, d_in, y=y,
-                                                       accumulate=acc), ref, bound, n, d_out)
+    lists = [upload(v) for v in (mx, mn, r)]
+    check(rows_call(fused, lists, w_idx, lut, upload(s_w)), ref, bound, n, d_out)
+
+
+@pytest.mark.parametrize("n,d_in,d_out,k", [(40, 512, 300, 20), (70, 2048, 77, 300)])
+def test_compensate_rows_sums_in_list_order(n, d_in, d_out, k):
+    """outlier_compensate_rows: one fp32 fma per entry in list order, then s_j, bit
+    for bit (each fma emulated in fp64 as one rounding of an exact sum: entries
+    of 13 bits and one magnitude, where the product has 24 bits)."""
+    print(f"case list order n={n} d_in={d_in} d_out={d_out} k={k}", flush=True)
+    w_idx, cb, s_w, mx, mn, r = inputs(n, d_in, d_out, k)
+    rng = np.random.default_rng(k)
+    r = (rng.integers(4096, 8192, r.shape) * rng.choice([-1.0, 1.0], r.shape) / 4096).astype(np.float32)
+    r[n // 2] = 0.0
+    ch, acc = np.concatenate([mx, mn], 1), np.zeros((n, d_out), dtype=np.float32)
+    c = cb.astype(np.float64)
+    for e in range(2 * k):
+        live = ch[:, e] >= 0
+        step = acc[live] + r[live, e, None].astype(np.float64) * c[w_idx[ch[live, e]]]
+        acc[live] = step.astype(np.float32)
+    lut = oasis.build_lut(np.arange(16).astype(np.float16), 4, cb, 4)
+    y = torch.full((n, d_out), float("nan"), device="cuda:0")
+    rows_call(False, [upload(v) for v in (mx, mn, r)], w_idx, lut, upload(s_w))(y, False)
+    torch.cuda.synchronize()
+    assert np.array_equal(y.cpu().numpy(), acc * s_w)
 
 
 @pytest.mark.parametrize("n,d_in,d_out,k", [
@@ -133,7 +170,8 @@ def test_small_entries_beside_a_massive_one(n, d_in, d_out, k):
 
 
 @pytest.mark.parametrize("n,d_in,d_out,k", [(33, 256, 100, 4), (800, 256, 6700, 3)])
-def test_infinite_residual_rows(n, d_in, d_out, k):
+@pytest.mark.parametrize("fused", [True, False])
+def test_infinite_residual_rows(n, d_in, d_out, k, fused):
     """An infinite residual gives infinities with its weights' signs; the other
     tokens of its tile stay as they are."""
     print(f"case compensate_mm inf n={n} d_in={d_in} d_out={d_out} k={k}", flush=True)
@@ -143,9 +181,8 @@ def test_infinite_residual_rows(n, d_in, d_out, k):
     ref, bound = reference(mx, mn, r, cb.astype(np.float64)[w_idx], s_w.astype(np.float64))
     r[10, 0] = np.inf
     lut = oasis.build_lut(cb, 4, cb, 4)
-    y = oasis.outlier_compensate_rows(upload(mx), upload(mn), upload(r),
-                                      upload(oasis.pack_weight_rows(w_idx).view(np.int32)), lut, 4,
-                                      upload(s_w), d_in, accumulate=False)
+    y = torch.full((n, d_out), float("nan"), device="cuda:0")
+    rows_call(fused, [upload(v) for v in (mx, mn, r)], w_idx, lut, upload(s_w))(y, False)
     torch.cuda.synchronize()
     got = y.cpu().numpy().astype(np.float64)
     assert np.array_equal(got[10], np.inf * np.sign(cb.astype(np.float64)[w_idx[mx[10, 0]]]))
