@@ -50,7 +50,9 @@ __global__ void __launch_bounds__(256) k_compensate(CompArgs A) {
       }
       const bool live = p >= 0 && p < d_in && r[u] != 0.0f;  // wave-uniform
       if (!live) r[u] = 0.0f;
-      sh[u] = live ? 4 * (p & 7) : 0;
+      // (no select on `live`: one made every entry a branch of its own, 12.6 ->
+      // 13.3 us at 4 x 4096 x 1024, k = 128)
+      sh[u] = 4 * (p & 7);
       w[u] = 0u;
       if (live && j < d_out) w[u] = A.idx_w[(size_t)(p >> 3) * d_out + j];
     }
