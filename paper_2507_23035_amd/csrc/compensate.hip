@@ -5,13 +5,13 @@
 // are dequantized with the weight codebook (the Dequant Unit) and multiplied
 // by the residual (the MAC units), then merged into the main-branch output.
 //
-// k_compensate (up to 32 tokens): one workgroup per (token, 64 output
-// columns); its 4 waves split the token's 2k listed channels and are summed
-// through LDS.  A lane owns a column and issues the word loads of 16 listed
-// channels before using any of them.  Channel ids and residuals are
-// wave-uniform; zero residuals (channels already compensated through the max
-// list) are skipped.  k_compensate_cols (more tokens): a wave per token and 64
-// or 256 columns.  k_compensate_wr: the row layout.
+// k_compensate (up to 32 tokens, or long lists over few columns): one workgroup
+// per (token, 64 output columns); its 4 waves split the token's 2k listed
+// channels and are summed through LDS.  A lane owns a column and issues the
+// word loads of 16 listed channels before using any of them.  Channel ids and
+// residuals are wave-uniform; zero residuals (channels already compensated
+// through the max list) are skipped.  k_compensate_cols (more tokens): a wave
+// per token and 64 or 256 columns.  k_compensate_wr: the row layout.
 #include "common.h"
 
 namespace oasis {
@@ -541,8 +541,15 @@ hipError_t launch_compensate(const CompArgs& a, hipStream_t s) {
     if (a.accumulate) return hipSuccess;
     return launch_fill_zero(a.y, (size_t)a.n * a.d_out, s);
   }
-  if (a.n > 32) return launch_compensate_cols<false>(a, nullptr, s);
-  dim3 grid(a.n, (a.d_out + 63) / 64);
+  // More than 32 tokens: a wave per token and column slab, unless lists of 12
+  // and more leave its chain of entries longer than five workgroups a CU of
+  // k_compensate, whose waves take a quarter of the list each.  There and here
+  // (us): 64 x 64, k = 4 3.6 and 2.7, k = 32 4.7 and 6.5, k = 128 12.7 and 20.4;
+  // k = 32, 64 x 1024 (1024 workgroups) 6.0 and 6.6, 33 x 2048 (1056) 6.4 and
+  // 6.6, 64 x 1536 (1536) 7.2 and 6.7, 64 x 4096 20.1 and 8.5
+  const dim3 grid(a.n, (a.d_out + 63) / 64);
+  if (a.n > 32 && (a.k < 12 || (long)grid.x * grid.y > 5l * device_cus()))
+    return launch_compensate_cols<false>(a, nullptr, s);
   hipLaunchKernelGGL(k_compensate, grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }

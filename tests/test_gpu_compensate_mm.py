@@ -192,7 +192,8 @@ def test_infinite_residual_rows(n, d_in, d_out, k, fused):
 
 @pytest.mark.parametrize("n,d_in,d_out,k", [
     (33, 64, 7, 2),           # one column a lane, most lanes past d_out
-    (100, 520, 130, 40),      # 80 entries: a second pass of 16
+    (100, 520, 130, 40),      # a workgroup per token and 64 columns: 20 entries a wave
+    (700, 520, 130, 40),      # one column a lane, 80 entries: a second pass of 16
     (2100, 264, 260, 3),      # four columns a lane, 16-byte stores, a partial slab
     (700, 256, 777, 33),      # four columns a lane, unaligned rows, 66 entries
 ])
