@@ -210,7 +210,8 @@ hipError_t launch_inlier_codes(const QuantArgs& a, hipStream_t s);
 // CUs of the current device
 int device_cus();
 // the matrix-core GEMM with the reduction split over a workgroup's waves (no
-// lists): its best tile for a size and that tile's estimated time
+// lists): its best tile (32 x 32, 64 x 64, 128 x 64, 128 x 128 columns x tokens)
+// for a size and that tile's estimated time
 struct KsPlan {
   int variant;
   float us;
@@ -223,6 +224,11 @@ hipError_t launch_gemm_ks_heavy(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_ks_percol(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_lut(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
+// the kernel launch_gemm_mfma takes for a size (exported for the dispatch's tests;
+// not part of the C ABI): the few-token one, a tile of the split reduction
+// (kRouteKs + plan_ks's variant), the many-token tiles, or k_gemm_mfma_prefill
+enum { kRouteGemv = 0, kRouteKs = 1, kRouteTiles = 5, kRoutePrefill = 6 };
+extern "C" int oasis_gemm_route(int n, int d_in, int d_out);
 // per-output-channel weight codebooks (a.cb_cols), n <= 32
 hipError_t launch_gemm_percol(const GemmArgs& a, hipStream_t s);
 // Y (+)= Y* + Y' in one launch when a.n <= kFusedMaxTokens.

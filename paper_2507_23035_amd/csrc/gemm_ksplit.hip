@@ -362,39 +362,48 @@ static hipError_t launch_ks_one(const GemmArgs& a, hipStream_t s) {
   const int ncx = (a.d_out + 32 * CW - 1) / (32 * CW), nty = (a.n + 32 * FT - 1) / (32 * FT);
   // the per-column table belongs to one tile
   const int grid = PERCOL ? ncx * nty : min(ncx * nty, device_cus());
-  if constexpr (HV)  // whole blocks only
-    hipLaunchKernelGGL((k_gemm_mfma_ks<CW, FT, NW, false, PERCOL, true>), dim3(grid),
+  if (HV || a.d_in % 64 == 0)
+    hipLaunchKernelGGL((k_gemm_mfma_ks<CW, FT, NW, false, PERCOL, HV>), dim3(grid),
                        dim3(NW * 64), 0, s, a, ncx, nty);
-  else if (a.d_in % 64 == 0)
-    hipLaunchKernelGGL((k_gemm_mfma_ks<CW, FT, NW, false, PERCOL, false>), dim3(grid),
-                       dim3(NW * 64), 0, s, a, ncx, nty);
+  else if constexpr (HV || CW * FT == 16)  // whole blocks only (plan_ks)
+    return hipErrorInvalidValue;
   else
     hipLaunchKernelGGL((k_gemm_mfma_ks<CW, FT, NW, true, PERCOL, false>), dim3(grid),
                        dim3(NW * 64), 0, s, a, ncx, nty);
   return hipGetLastError();
 }
 
-// The tile by its estimated time: rounds of one tile per CU, each a fixed part
-// (reduction, prologue) and a part per 4096 channels, fitted to timings
-// (us, one round each: 32 x 32 4.3 at d_in = 4096 and 7.8 at 8192, 64 x 64 10
-// and 18, 128 x 64 17 and 30, 128 x 128 32 and 58).  Small tiles fill the
-// CUs, large ones expand fewer operands per MFMA.
+// The tile by its estimated time: a + b k4 + rounds (f + p k4) us, k4 = d_in /
+// 4096, a round being one tile per CU.  Fitted to every tile at 91 sizes (n 64
+// to 4000, d_out 2080 to 20000, d_in 256 to 8192) and, for the masked kernels
+// (d_in not a multiple of 64: offsets per load), at 116 (n 40 to 4000, d_out 700
+// to 20000, d_in 136 to 8200); b < 0 because a first round is shorter than the
+// ones that start under another tile's reduction.  With many_token_us the
+// choice takes 0.4 % (masked 0.2 %) more than the fastest kernel on average,
+// 8 % at most, and at one size more than the many-token kernel where that is
+// faster (2.5 % at 1000 x 8200 x 8100).
+// Small tiles fill the CUs, large ones expand fewer operands per MFMA; the
+// masked 128 x 128 tile was never the fastest and is not built.
 KsPlan plan_ks(int n, int d_in, int d_out, bool heavy) {
-  struct Tile { int cols, toks; float fix, per4k; };
-  // the masked kernels (d_in not a multiple of 64) add offsets per load
+  struct Tile { int cols, toks; float a, b, f, p; };
+  static const Tile whole[4] = {{32, 32, 2.9f, 0.0f, 1.3f, 3.0f},
+                                {64, 64, 2.5f, -0.7f, 2.4f, 7.6f},
+                                {128, 64, 2.5f, -2.7f, 4.5f, 13.1f},
+                                {128, 128, 2.8f, -6.7f, 6.5f, 27.4f}};
+  static const Tile masked[3] = {{32, 32, 2.7f, 0.1f, 1.4f, 3.1f},
+                                 {64, 64, 2.7f, -1.0f, 2.6f, 8.7f},
+                                 {128, 64, 2.9f, -2.5f, 4.5f, 15.2f}};
   const bool mask = d_in % 64 != 0;
-  const Tile tiles[4] = {{32, 32, 0.8f, 3.5f},
-                         {64, 64, 2.0f, 8.0f},
-                         {128, 64, 3.5f, 13.5f},
-                         {128, 128, mask ? 8.0f : 6.0f, mask ? 29.0f : 26.0f}};
+  const Tile* tiles = mask ? masked : whole;
   const float k4 = (float)d_in / 4096.0f;
+  const long cus = device_cus();
   KsPlan best{0, 0.0f};
   const int v0 = heavy ? 3 : 0;  // heavy blocks: 128 x 128 only
-  for (int v = v0; v < 4; ++v) {
-    const long t = (long)((d_out + tiles[v].cols - 1) / tiles[v].cols) *
-                   ((n + tiles[v].toks - 1) / tiles[v].toks);
-    const long rounds = (t + 255) / 256;
-    const float us = 3.0f + (float)rounds * (tiles[v].fix + tiles[v].per4k * k4);
+  for (int v = v0; v < (mask ? 3 : 4); ++v) {
+    const Tile& q = tiles[v];
+    const long t = (long)((d_out + q.cols - 1) / q.cols) * ((n + q.toks - 1) / q.toks);
+    const long rounds = (t + cus - 1) / cus;
+    const float us = q.a + q.b * k4 + (float)rounds * (q.f + q.p * k4);
     if (v == v0 || us < best.us) best = KsPlan{v, us};
   }
   return best;

@@ -1326,38 +1326,57 @@ hipError_t launch_gemm_values(const GemmArgs& a, hipStream_t s) {
 
 // Workgroup tile 256 x 256 (2 x 2 waves of 128 x 128, 256 accumulator
 // registers per lane: one wave per SIMD) when the grid fills at least three
-// rounds of the 256 CUs, else 256 x 128 (waves of 128 x 64, two workgroups
-// and two waves per SIMD on a CU).  Needs d_in % 64 == 0 (whole blocks of 64
-// channels).
+// rounds of the CUs, else 256 x 128 (waves of 128 x 64, two workgroups and two
+// waves per SIMD on a CU).  Needs d_in % 64 == 0 (whole blocks of 64 channels).
+static bool many_tokens_256(int n, int d_out) {
+  return (long)((d_out + 255) / 256) * ((n + 255) / 256) >= 3l * device_cus();
+}
 template <bool HV = false>
 static hipError_t launch_gemm_tiles(const GemmArgs& a, hipStream_t s) {
-  const long t44 = (long)((a.d_out + 255) / 256) * ((a.n + 255) / 256);
-  if (t44 >= 3 * 256) return launch_tile<4, 4, 2, 2, false, HV>(a, s);
+  if (many_tokens_256(a.n, a.d_out)) return launch_tile<4, 4, 2, 2, false, HV>(a, s);
   return launch_tile<4, 2, 2, 2, false, HV>(a, s);
 }
 
-// Estimated time of the many-token kernels (us) against plan_ks: their tiles
-// over 256 CUs, a fixed part and a part per 4096 channels each, fitted to
-// timings.  256 x 256 tiles: 206 per round at d_in = 8192; 256 x 128, two a
-// CU: 30 each at 2048, 57 to 60 at 4096, 74 there where a CU has only one; 128 x 128 (d_in not a
-// multiple of 64): 41 at 4104 and 72 at 8200.
+// Estimated time of the many-token kernels (us) against plan_ks, fitted to the
+// sizes named there; t: tiles per CU, k4 = d_in / 4096.
+//  - d_in not a multiple of 64 (128 x 128 tiles, two workgroups a CU): 8.5 + 46
+//    k4 for the first tile of a CU, part of a second costs almost half of it at
+//    once, each later one 3.7 + 33.5 k4;
+//  - 256 x 128 tiles, two workgroups a CU: 52 k4 a tile where a quarter of the
+//    CUs have none, 62 where all have one, 39 to 51 each where some have two, 54
+//    from three on;
+//  - 256 x 256 tiles: 100 k4 a round.
+// Rows of y that are not whole 16-byte pieces are stored by elements.
 static float many_token_us(int n, int d_in, int d_out) {
-  const float k4 = (float)d_in / 4096.0f;
-  auto tiles = [&](int cols, int toks) {
-    return (long)((d_out + cols - 1) / cols) * ((n + toks - 1) / toks);
+  const float k4 = (float)d_in / 4096.0f, cus = (float)device_cus();
+  auto per_cu = [&](int cols, int toks) {
+    return (float)((long)((d_out + cols - 1) / cols) * ((n + toks - 1) / toks)) / cus;
   };
-  if (d_in % 64 != 0)
-    return 3.0f + max(1.4f, (float)tiles(128, 128) / 256.0f) * (6.0f + 35.0f * k4);
-  const long t44 = tiles(256, 256);
-  if (t44 >= 3 * 256) return 3.0f + (float)((t44 + 255) / 256) * (5.0f + 100.0f * k4);
-  const long per_cu = (tiles(256, 128) + 255) / 256;
-  return 3.0f + (float)per_cu * (5.0f + (per_cu == 1 ? 66.0f : 54.0f) * k4);
+  float us;
+  if (d_in % 64 != 0) {
+    const float t = per_cu(128, 128);
+    us = 8.5f + 46.0f * k4;
+    if (t > 1.0f) us += (0.4f + 0.6f * min(t - 1.0f, 1.0f)) * (5.5f + 19.0f * k4);
+    if (t > 2.0f) us += (ceilf(t) - 2.0f) * (3.7f + 33.5f * k4);
+  } else if (many_tokens_256(n, d_out)) {
+    us = 3.0f + ceilf(per_cu(256, 256)) * (5.0f + 100.0f * k4);
+  } else {
+    const float t = per_cu(256, 128), c = ceilf(t);
+    const float each = c <= 1.0f ? (t <= 0.75f ? 52.0f : 62.0f)
+                                 : c <= 2.0f ? 39.0f + 12.0f * (t - 1.0f) : 54.0f;
+    us = 3.0f + c * (5.0f + each * k4);
+  }
+  return us + (d_out % 4 ? 4.2e-6f * (float)n * (float)d_out : 0.0f);
 }
+
+// Within 2 % the many-token kernels: 4025 x 2368 x 2048, estimates 43.6 and
+// 43.8, takes 51.8 us with the reduction split and 48.9 without.
+constexpr float kTie = 1.02f;
 
 // (the heavy blocks add the same to both: 2048 x 11008 x 4096, 195 us with
 // 256 x 128 tiles, one a CU, 166 with 128 x 128 split over the waves)
 hipError_t launch_gemm_heavy(const GemmArgs& a, hipStream_t s) {
-  if (plan_ks(a.n, a.d_in, a.d_out, true).us < many_token_us(a.n, a.d_in, a.d_out))
+  if (kTie * plan_ks(a.n, a.d_in, a.d_out, true).us < many_token_us(a.n, a.d_in, a.d_out))
     return launch_gemm_ks_heavy(a, s);
   return launch_gemm_tiles<true>(a, s);
 }
@@ -1522,15 +1541,22 @@ static void launch_gemv_tf(const GemmArgs& a, hipStream_t s) {
   }
 }
 
+extern "C" int oasis_gemm_route(int n, int d_in, int d_out) {
+  if (n <= 32) return kRouteGemv;
+  const KsPlan ks = plan_ks(n, d_in, d_out);
+  if (kTie * ks.us < many_token_us(n, d_in, d_out)) return kRouteKs + ks.variant;
+  return d_in % 64 == 0 ? kRouteTiles : kRoutePrefill;
+}
+
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
   if (a.n <= 16) {
     launch_gemv_tf<1>(a, s);
   } else if (a.n <= 32) {
     launch_gemv_tf<2>(a, s);
   } else {
-    const KsPlan ks = plan_ks(a.n, a.d_in, a.d_out);
-    if (ks.us < many_token_us(a.n, a.d_in, a.d_out)) return launch_gemm_ks(a, ks.variant, s);
-    if (a.d_in % 64 == 0) return launch_gemm_tiles(a, s);
+    const int r = oasis_gemm_route(a.n, a.d_in, a.d_out);
+    if (r < kRouteTiles) return launch_gemm_ks(a, r - kRouteKs, s);
+    if (r == kRouteTiles) return launch_gemm_tiles(a, s);
     launch_prefill<4, 4, 2, 2>(a, s);
   }
   return hipGetLastError();
