@@ -313,8 +313,8 @@ int oasis_outlier_compensate_split(const int32_t* max_idx, const int32_t* min_id
  *   workspace of oasis_outlier_compensate_split (the same size query,
  *   oasis_outlier_compensate_split_workspace(n, d_in, d_out, k)).
  *   n <= 32 tokens or k == 0: the call of oasis_lut_gemm_compensated_rows
- *   (no workspace needed).  Up to 10^9 list entries x columns
- *   (2 n k d_out) the lists are compensated whole, after the GEMM (the
+ *   (no workspace needed).  Below 400 tokens, and up to 10^9 list entries x
+ *   columns (2 n k d_out), the lists are compensated whole, after the GEMM (the
  *   workspace is checked, not used).  Beyond that, d_in not a multiple of 64:
  *   the split compensation, then the GEMM, two passes over y.
  * Errors: NULL, SHAPE, BITS, K, ALIGN, TOO_LARGE, WORKSPACE, LAUNCH.

@@ -407,11 +407,16 @@ int oasis_lut_gemm_compensated_split(const uint8_t* idx_act, const float* act_sc
   if (!workspace || !aligned(workspace, 256) ||
       workspace_bytes < oasis::split_layout(n, d_in, d_out, k).total)
     return OASIS_ERR_WORKSPACE;
-  // Few products of lists and columns: the prepass (four launches, 19 us and
-  // more) and the heavy blocks cost more than they take off the lists (about
-  // 0.07 us per 10^6 entries x columns).  At 2048 x 4096 x 11008 with k = 32,
-  // 1.4e9, both ways take the same.
-  if ((uint64_t)n * 2u * (uint64_t)k * (uint64_t)d_out <= 1000000000ull)
+  // Few products of lists and columns, or few tokens: the prepass (four
+  // launches, 19 us and more), the heavy blocks and the larger tiles they need
+  // cost more than they take off the lists.  Whole lists and split (us):
+  //   4096 x 4096, k = 32     n = 1024 65, 73   2048 107, 115  4096 (1.07e9) 195, 193
+  //   4096 x 11008, k = 32    n = 512 80, 105   1400 (0.99e9) 190, 187  2048 272, 263
+  //   8192 x 8192, k = 64     n = 512 114, 117  1024 (1.07e9) 191, 186  4096 704, 641
+  //   8192 x 28672, k = 64    n = 136 134, 160  300 (1.10e9) 222, 233   512 343, 328
+  //   11008 x 4096, k = 88    n = 1024 131, 146 1400 (1.01e9) 185, 227  2048 254, 243
+  //   8384 x 25728, k = 252   n = 136 (1.76e9) 218, 308
+  if (n < 400 || (uint64_t)n * 2u * (uint64_t)k * (uint64_t)d_out <= 1000000000ull)
     return gemm_compensated(idx_act, act_scale, n, d_in, idx_w, idx_wr, w_scale, d_out, lut, b_a,
                             b_w, max_idx, min_idx, residual, k, y, accumulate, stream);
   oasis::GemmArgs g{idx_act, act_scale, n, d_in, idx_w, w_scale, d_out, lut, b_a, b_w, y, 1,
