@@ -267,8 +267,11 @@ def test_percol_error_of_one_gemm(n, d_in, d_out, k):
 @pytest.mark.parametrize("n,d_in,d_out,k,mode", [
     (2000, 256, 4000, 64, O.SCALE_NONE),    # residuals over t past 2^15 leave the GEMM
     (1100, 1088, 2000, 256, O.SCALE_ABSMAX),  # more heavy channels than the dense part takes
+    (2000, 264, 4000, 64, O.SCALE_ABSMAX),  # d_in not a multiple of 64: split, then the GEMM
+    (400, 320, 16101, 80, O.SCALE_ABSMAX),  # the fewest tokens, unaligned rows of y
 ])
-def test_split_is_taken(n, d_in, d_out, k, mode):
+@pytest.mark.parametrize("accumulate", [False, True])
+def test_split_is_taken(n, d_in, d_out, k, mode, accumulate):
     """The split by channel inside the GEMM, at sizes past the rule that skips it."""
     assert n * 2 * k * d_out > 10 ** 9
     L = synth.make_layer(synth.custom(n, d_in, d_out, k, seed=77, dist="normal", outlier_count=5,
@@ -285,9 +288,10 @@ def test_split_is_taken(n, d_in, d_out, k, mode):
     lut = oasis.build_lut(L.cb_a, 4, L.cb_w, 4)
     ws = torch.full((oasis.split_workspace_bytes(n, d_in, d_out, k),), 0x5A, dtype=torch.uint8,
                     device=dev)
-    y = oasis.lut_gemm_compensated_split(t(O.pack_act_indices(q["a"])), t(q["t"]), idx_w, idx_wr,
-                                         t(L.s_w), lut, 4, 4, t(q["max_idx"]), t(q["min_idx"]),
-                                         t(q["residual"]), workspace=ws)
+    y = torch.full((n, d_out), 0.5 if accumulate else float("nan"), device=dev)
+    oasis.lut_gemm_compensated_split(t(O.pack_act_indices(q["a"])), t(q["t"]), idx_w, idx_wr,
+                                     t(L.s_w), lut, 4, 4, t(q["max_idx"]), t(q["min_idx"]),
+                                     t(q["residual"]), y=y, accumulate=accumulate, workspace=ws)
     torch.cuda.synchronize()
     w = L.cb_w.astype(np.float64)[L.w_idx]
     a = L.cb_a.astype(np.float64)[q["a"]] * q["t"].astype(np.float64)[:, None]
@@ -296,6 +300,9 @@ def test_split_is_taken(n, d_in, d_out, k, mode):
     main = (torch.from_numpy(a) @ torch.from_numpy(w)).numpy() * L.s_w
     mag = (torch.from_numpy(np.abs(a)) @ torch.from_numpy(np.abs(w))).numpy() * L.s_w
     bound = bound + 2.0 * (d_in + 2) * 2.0 ** -24 * mag
+    if accumulate:  # 0.5 added once, one more rounding
+        main = main + 0.5
+        bound = bound + 2.0 ** -23 * (np.abs(main + comp) + 0.5)
     err = np.abs(y.cpu().numpy().astype(np.float64) - main - comp)
     assert np.all(err <= bound), (err / bound).max()
 

@@ -16,12 +16,15 @@ def token_variants(x):
 
 
 @pytest.mark.parametrize("schedule", ["fused", "fused_percol", "separate", "lookahead", "split",
-                                      "split_noalloc"])
+                                      "split_noalloc", "split_heavy", "split_heavy_noalloc"])
 def test_graph_replays_match_eager(schedule):
     name = "decode_8x4096x4096" if schedule.startswith("fused") else None
     if name:
         spec = synth.config(name)
-    elif schedule.startswith("split"):   # d_in a multiple of 64: heavy channels in the GEMM
+    elif schedule.startswith("split_heavy"):   # past 10^9 entries x columns: heavy channels
+        spec = synth.custom(2000, 256, 4000, 64, seed=73)  # in the GEMM, the scratch in use
+        assert spec.n * 2 * spec.k * spec.d_out > 10 ** 9
+    elif schedule.startswith("split"):   # whole lists
         spec = synth.custom(70, 1024, 300, 20, seed=72)
     else:
         spec = synth.custom(70, 1032, 300, 20, seed=71)
@@ -63,11 +66,11 @@ def test_graph_replays_match_eager(schedule):
             oasis.lut_gemm_compensated_rows(q["idx_act"], q["act_scale"], idx_w, idx_wr, s_w, lut,
                                             s.b_a, s.b_w, q["max_idx"], q["min_idx"],
                                             q["residual"], y=y)
-        elif schedule == "split":
+        elif schedule in ("split", "split_heavy"):
             oasis.lut_gemm_compensated_split(q["idx_act"], q["act_scale"], idx_w, idx_wr, s_w, lut,
                                              s.b_a, s.b_w, q["max_idx"], q["min_idx"],
                                              q["residual"], y=y, workspace=ws)
-        elif schedule == "split_noalloc":
+        elif schedule.endswith("noalloc"):
             st = lib.oasis_lut_gemm_compensated_split_noalloc(
                 q["idx_act"].data_ptr(), q["act_scale"].data_ptr(), s.n, s.d_in,
                 idx_w.data_ptr(), idx_wr.data_ptr(), s_w.data_ptr(), s.d_out, lut.data_ptr(),

@@ -219,13 +219,14 @@ RAGGED = [
     (130, 136, 129, 5, 4, 4, 7),
     (40, 4096, 200, 32, 1, 1, 8),
     (64, 520, 512, 16, 4, 2, 9),
-    (72, 1032, 260, 300, 4, 4, 14),  # row-grouped compensation: 6 tokens per tile
-    (70, 4096, 96, 2048, 4, 4, 15),  # one token per tile
-    (66, 4104, 40, 2050, 4, 4, 16),  # lists too long for a tile: per-token kernel
+    (72, 1032, 260, 300, 4, 4, 14),  # lists longer than a wave of any lists kernel holds
+    (70, 4096, 96, 2048, 4, 4, 15),  # k = d_in / 2
+    (66, 4104, 40, 2050, 4, 4, 16),  # and more: channels on both lists
     (64, 1024, 136, 256, 4, 4, 18),  # ~512 channels listed by every token: more heavy
-                                     # channels than the dense part takes (256)
-    (40, 20544, 72, 64, 4, 4, 19),   # more channels than the split's LDS counts hold:
-                                     # global counts, selection in a launch of its own
+                                     # channels than the dense part of the split
+                                     # compensation takes (256)
+    (40, 20544, 72, 64, 4, 4, 19),   # more channels than its LDS counts hold: global
+                                     # counts, selection in a launch of its own
 ]
 
 
@@ -272,9 +273,10 @@ def test_gemv_balanced_tiles(n, d_in, d_out, k, b_a, b_w, seed):
 
 def test_split_heavy_channels_out_of_range():
     """Scale mode NONE (t = 1) with a channel of +-40000 in every token: its
-    residual over t cannot be an fp16 hi/lo pair below 2^15, so the GEMM with
-    the heavy channels must hand it to the lists; 64 tokens (the many-token
-    path), d_in a multiple of 64 (the heavy phase inside the GEMM)."""
+    residual is far beyond fp16, in the split compensation (scaled per token) and
+    in whole lists, which the fused calls take at 64 tokens.  (The GEMM's heavy
+    phase, which has to hand such a channel to the lists, starts at 400 tokens:
+    test_split_is_taken.)"""
     L = synth.make_layer(synth.custom(64, 256, 136, 4, seed=19, dist="normal",
                                       outlier_count=3, outlier_scale=6.0))
     x = L.x.copy()
@@ -300,7 +302,7 @@ PERCOL = [
     (70, 520, 100, 8, 64),       # three 32-token launches, the last one of 6 tokens
     (49, 264, 48, 2, 65),        # a 17-token second launch (two token tiles)
     "large_decode_16x8192x28672",
-    "prefill_up_2048x4096x11008",  # 64 launches; sampled rows
+    "prefill_up_2048x4096x11008",  # one GEMM, then the compensation; sampled rows
 ]
 
 
@@ -600,7 +602,7 @@ def test_persistent_tiles_ragged():
 
 @pytest.mark.parametrize("case", [
     (3000, 512, 16400, 16, 61),   # 256 x 256 tiles: 12 token tiles, groups of 8 and 4
-    (1100, 1032, 5000, 16, 62),   # 256 x 128 tiles: 9 token tiles, groups of 8 and 1
+    (1100, 1032, 5000, 16, 62),   # 128 x 128 tiles (d_in not a multiple of 64): 9 token tiles
 ], ids=str)
 def test_grouped_tile_order(case):
     """The many-token GEMM numbers its tiles in groups of 8 token tiles; a

@@ -1,6 +1,8 @@
 """The no-allocation entry point against the workspace one, through the C ABI:
-two calls in a row (the second smaller, over the scratch the first left),
-each within the parity bound of the other; and the size limit."""
+calls in a row (smaller ones over the scratch the one before left), each within
+the parity bound of the other; and the size limit.  The scratch is read and
+written from 400 tokens and 10^9 list entries x columns on; smaller calls
+compensate whole lists."""
 import ctypes
 
 import numpy as np
@@ -61,9 +63,24 @@ def test_no_alloc_matches_workspace_entry_point():
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     lib = oasis.load()
-    run_case(lib, 300, 1024, 520, 24, 71)   # heavy channels inside the GEMM
-    run_case(lib, 70, 512, 136, 8, 72)      # smaller, over the scratch the first call left
-    run_case(lib, 40, 264, 100, 5, 73)      # d_in not a multiple of 64: split, then the GEMM
+    run_case(lib, 300, 1024, 520, 24, 71)   # whole lists: the scratch is not used
+    run_case(lib, 70, 512, 136, 8, 72)
+    run_case(lib, 40, 264, 100, 5, 73)      # d_in not a multiple of 64
+
+
+@pytest.mark.parametrize("cases", [
+    # heavy channels inside the GEMM, then fewer tokens over what that call left
+    [(2000, 256, 4000, 64), (410, 256, 19000, 70)],
+    # d_in not a multiple of 64: split compensation, then the GEMM adding to it
+    [(410, 256, 19000, 70), (2000, 264, 4000, 64)],
+])
+def test_no_alloc_uses_its_scratch(cases):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    lib = oasis.load()
+    for n, d_in, d_out, k in cases:
+        assert n >= 400 and 2 * n * k * d_out > 10 ** 9
+        run_case(lib, n, d_in, d_out, k, 74)
 
 
 def test_no_alloc_rejects_sizes_beyond_its_scratch():
