@@ -90,17 +90,19 @@ def call_bytes(n, d_in, d_out, k, path):
     }
 
 
+_QUANT = ["quantize.hip"]
+_GEMM = ["lut_gemm.hip", "gemm_ksplit.hip", "decode_table.h"]
+_LISTS = ["compensate.hip", "compensate_mm.hip"]
 KERNEL_SOURCES = {
     "build_lut": ["lut.hip"],
-    "quantize_act": ["quantize.hip"], "cluster_act": ["quantize.hip"],
-    "build_lut_quantize_act": ["quantize.hip"], "quantize_act_static": ["quantize.hip"],
-    "build_lut_quantize_act_static": ["quantize.hip"],
-    "detect_outliers": ["quantize.hip"],
-    "outlier_compensate": ["compensate.hip", "split.hip", "lut_gemm.hip"],
-    "lut_gemm": ["lut_gemm.hip"], "lut_gemm_compensated": ["lut_gemm.hip", "compensate.hip"],
-    "lut_gemm_compensated_rows": ["lut_gemm.hip", "compensate.hip"],
-    "lut_gemm_compensated_split": ["lut_gemm.hip", "compensate.hip", "split.hip"],
-    "lut_gemm_compensated_percol": ["lut_gemm.hip"],
+    "quantize_act": _QUANT, "cluster_act": _QUANT, "build_lut_quantize_act": _QUANT,
+    "quantize_act_static": _QUANT, "build_lut_quantize_act_static": _QUANT,
+    "detect_outliers": _QUANT,
+    "outlier_compensate": _LISTS + ["split.hip"] + _GEMM,
+    "lut_gemm": _GEMM, "lut_gemm_compensated": _GEMM + ["compensate.hip"],
+    "lut_gemm_compensated_rows": _GEMM + _LISTS,
+    "lut_gemm_compensated_split": _GEMM + _LISTS + ["split.hip"],
+    "lut_gemm_compensated_percol": _GEMM + ["compensate.hip"],
 }
 
 

@@ -1,13 +1,20 @@
 """The GEMM kernel chosen for a size, without a GPU (256 CUs are assumed there):
 the GPU cases run the kernel they are listed under, and sizes whose kernels were
-timed go to the fastest or, within the estimate's error, next to it."""
+timed go to the fastest or, within the estimate's error, next to it.  And the sources a call's
+counters are tied to."""
+import os
+import re
+
 import pytest
 
+import bench
 import test_gpu_ksplit as K
-from paper_2507_23035_amd import oasis
+from paper_2507_23035_amd import build, oasis
 
 
 def route(n, d_in, d_out):
+    if not os.path.exists(oasis.LIB_PATH):
+        build.build()
     return oasis.load().oasis_gemm_route(n, d_in, d_out)
 
 
@@ -38,3 +45,15 @@ TIMED = [
 def test_timed_sizes(n, d_in, d_out, us):
     r = route(n, d_in, d_out)
     assert us[0 if r >= K.TILES else r] <= 1.09 * min(u for u in us if u)
+
+
+def test_counters_are_tied_to_every_kernel_source():
+    """bench.py drops counters once a source of the call's kernels has changed: each
+    HIP source belongs to a call, and a listed one brings its headers along."""
+    listed = set().union(*bench.KERNEL_SOURCES.values())
+    assert {f for f in build.SOURCES if f.endswith(".hip")} <= listed
+    for call, files in bench.KERNEL_SOURCES.items():
+        for f in files:
+            text = open(os.path.join(build.CSRC, f)).read()
+            included = set(re.findall(r'#include "(\w+\.h)"', text)) - {"common.h", "oasis.h"}
+            assert included <= set(files), (call, f)
