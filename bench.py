@@ -173,9 +173,11 @@ def summarize_pmc(root, workload, path):
         for c, sub in (("FETCH_SIZE", "fetch"), ("WRITE_SIZE", "write")):
             rs = [r for r in _pmc_rows(os.path.join(root, sub), c) if sym in r["Kernel_Name"]]
             if call == "lut_gemm":  # the main-branch kernel alone: a tile kernel's value
-                # operand and heavy-block variants (5th and 6th template arguments) are not
+                # operand and heavy-block variants (5th and 6th template arguments) are
+                # not, nor the split reduction's with heavy blocks (6th)
                 rs = [r for r in rs if not re.search(
-                    r"k_gemm_mfma_tile<\d+, \d+, \d+, \d+, (true, \w+|\w+, true)",
+                    r"k_gemm_mfma_tile<\d+, \d+, \d+, \d+, (true, \w+|\w+, true)"
+                    r"|k_gemm_mfma_ks<\d+, \d+, \d+, \w+, \w+, true",
                     r["Kernel_Name"])]
             if call in ("cluster_act", "detect_outliers", "quantize_act",
                         "build_lut_quantize_act"):

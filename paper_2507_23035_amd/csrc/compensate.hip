@@ -81,10 +81,9 @@ __global__ void __launch_bounds__(256) k_compensate(CompArgs A) {
 // PERCOL: the LDS holds every column's own codebook.
 //
 // Entries alternate between the two lists from their last, smallest, ones on,
-// and each place of a unit has a sum of its own: the error against 64 bits of
-// a pass of 512 x 4096 x 4096 with per-column codebooks is 1.5e-7 instead of
-// 1.6e-7 for one sum in list order, at the same time (1.3e-7 with the
-// compensation inside the GEMV kernel).
+// and each place of a unit has a sum of its own: at 512 x 4096 x 4096 with
+// per-column codebooks Y' is off by 6.5e-8 against 64 bits (9.2e-8 with the
+// compensation inside the GEMV kernel), at the time of one sum in list order.
 //
 // Bound by VALU issue (3.5 instructions per entry and column at CPL = 4) and
 // by the word reads, 4 bytes per entry and column.  It replaced a kernel that
@@ -526,8 +525,8 @@ static hipError_t launch_compensate_cols(const CompArgs& a, const uint16_t* cb_c
                        ntile, ncol);
     return hipGetLastError();
   };
-  // one column a lane while four would leave waves idle (8 waves a SIMD)
-  if ((long)a.n * ((a.d_out + 255) / 256) < 2048) return go(k_compensate_cols<1, PERCOL>, 64);
+  // one column a lane while four would give a CU fewer than 8 waves
+  if ((long)a.n * ((a.d_out + 255) / 256) < 8l * device_cus()) return go(k_compensate_cols<1, PERCOL>, 64);
   return go(k_compensate_cols<4, PERCOL>, 256);
 }
 
