@@ -85,8 +85,10 @@ __global__ void __launch_bounds__(256) k_compensate(CompArgs A) {
 // per-column codebooks Y' is off by 6.5e-8 against 64 bits (9.2e-8 with the
 // compensation inside the GEMV kernel), at the time of one sum in list order.
 //
-// Bound by VALU issue (3.5 instructions per entry and column at CPL = 4) and
-// by the word reads, 4 bytes per entry and column.  It replaced a kernel that
+// Bound by VALU issue (3.5 instructions per entry and column at CPL = 4: half of
+// the SIMDs' cycles at 777 x 5000 x 3001, where waves wait to issue 47 % of
+// their time; LDS active 22 %) and by the word reads, 4 bytes per entry and
+// column.  It replaced a kernel that
 // sorted the entries of 4 tokens by word row first: 512 x 4096 x 11008, k = 32
 // 87 -> 64 us, 777 x 5000 x 3001, k = 50 171 -> 52, 512 x 4096 x 4096 70 -> 25,
 // 2048 x 4096 x 11008 266 -> 219.  (16 tokens' rows as an MFMA operand: 92, 85

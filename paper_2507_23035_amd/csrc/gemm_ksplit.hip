@@ -11,10 +11,13 @@
 // A tile then costs 1 / (4 SIMDs) of its MFMAs per CU however small it is, so
 // it can be cut until the grid covers the CUs.
 //
-// What bounds it: matrix cores at 128 x 64 and 128 x 128 (per 16 channels a
-// 128 x 64 tile has 8 MFMAs of 32 clk on a SIMD against 24 table reads of 2
-// clk on the CU's LDS), table reads at 32 x 32 (8 reads for one MFMA); below
-// about 4096 channels the fixed part, i.e. launch, decode table and reduction.
+// What bounds it: per 16 channels a 128 x 64 tile has 8 MFMAs of 32 clk on a
+// SIMD against 24 table reads of 2 clk on the CU's LDS, a 32 x 32 tile one MFMA
+// against 8 reads.  By counters the matrix cores are busy 53 % of the time with
+// 128 x 128 tiles (2048 x 11008 x 4096), 40 % with 128 x 64 (200 x 8192 x 8192)
+// and 22 % with 64 x 64 (777 x 5000 x 3001), the LDS active 29, 36 and 27 %; the
+// rest is the fixed part (launch, decode table, reduction: a + f of plan_ks) and
+// waiting, a quarter to two fifths of the wave time.
 // Measured against the many-token kernel (us): 64 x 4096 x 4096 55.4 -> 7.4,
 // 200 x 8192 x 8192 109 -> 33, 512 x 4096 x 4096 57 -> 20, 2048 x 11008 x 4096
 // 185 -> 155, and, for d_in not a multiple of 64, 777 x 5000 x 3001 71 -> 40.
@@ -410,7 +413,8 @@ KsPlan plan_ks(int n, int d_in, int d_out, bool heavy) {
 }
 
 // 32 columns x 128 tokens: the table holds 32 columns' codebooks, the tokens
-// make up for it (512 x 4096 x 4096: 35.5 us against 54 at 32 x 64)
+// make up for it (512 x 4096 x 4096, one sum an output: 35.5 us against 54 at
+// 32 x 64)
 hipError_t launch_gemm_ks_percol(const GemmArgs& a, hipStream_t s) {
   return launch_ks_one<1, 4, 8, true>(a, s);
 }
