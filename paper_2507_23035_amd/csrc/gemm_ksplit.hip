@@ -340,8 +340,20 @@ __global__ void __launch_bounds__(NW * 64, NW / 4) k_gemm_mfma_ks(GemmArgs A, in
         const float ts = sc[32 * CW + 32 * f + rt];
         const float4_t sw = *reinterpret_cast<const float4_t*>(&sc[32 * c + 4 * x]);
         float4_t v = {0.f, 0.f, 0.f, 0.f};
+        if constexpr (PERCOL) {  // in pairs: three roundings instead of seven (the
+          // pass of 332 x 1152 x 2560 9.8e-8 -> 9.2e-8, in GEMV launches 9.7e-8)
+          float4_t p[NW];
 #pragma unroll
-        for (int w = 0; w < NW; ++w) v += red[(w * PT + t) * 256 + 32 * x + (rt ^ x)];
+          for (int w = 0; w < NW; ++w) p[w] = red[(w * PT + t) * 256 + 32 * x + (rt ^ x)];
+#pragma unroll
+          for (int d = NW / 2; d > 0; d /= 2)
+#pragma unroll
+            for (int w = 0; w < d; ++w) p[w] += p[w + d];
+          v = p[0];
+        } else {
+#pragma unroll
+          for (int w = 0; w < NW; ++w) v += red[(w * PT + t) * 256 + 32 * x + (rt ^ x)];
+        }
         float* dst = A.y + (size_t)tok * d_out + j;
         if (vec) {
           v = ts * sw * v;
