@@ -274,8 +274,7 @@ int oasis_outlier_compensate_rows(const int32_t* max_idx, const int32_t* min_idx
  * tokens (at most 256 of them, lowest channels first) are compensated
  * together as a dense contraction on the matrix cores (the residuals of a
  * token, scaled by a power of two, as an fp16 hi/lo pair per channel), every
- * other entry by the row-layout kernel of oasis_outlier_compensate_rows over
- * compacted per-token lists.  The result is Y' of oasis_outlier_compensate;
+ * other entry from the row layout over compacted per-token lists.  The result is Y' of oasis_outlier_compensate;
  * which channels count as heavy changes only the fp32 summation order.  (A
  * list naming a channel twice with nonzero residuals has both entries summed,
  * in an order that may vary between runs.)
@@ -391,8 +390,8 @@ int oasis_lut_gemm_compensated_rows(const uint8_t* idx_act, const float* act_sca
  * C_A x C_W[j] (the Cartesian product of Sec. III-B, built per 16-column
  * tile in LDS) and the compensation dequantizes with C_W[j] (Sec. III-C2);
  * s_j still scales column j.  A shared codebook is the case of equal rows
- * (for n <= 32 and fewer than 256 tiles of 32 columns, bit for bit the
- *   same y as oasis_lut_gemm_compensated; else up to fp32 summation order).
+ * (for n <= 32 and fewer than 256 tiles of 32 columns, bit for bit the same y
+ * as oasis_lut_gemm_compensated; else up to fp32 summation order).
  *   cb_wgt_cols : DEVICE fp16 [d_out][16], 16-byte aligned; entries past
  *                 2^b_w are read but never selected (any finite value).
  *   lut         : a LUT block built with the same b_a (its C_A is used).
